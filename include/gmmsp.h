@@ -482,8 +482,7 @@ int gmmsp_connectivity_static(gmmsp_handle* h, const float* lab_dev, const int32
  * output of gmmsp_label); gt_dev: int32 per pixel with values in
  * [0, n_gt_host[b]).  Workspace (caller-allocated, 256-byte aligned):
  * gmmsp_metrics_workspace_bytes, dominated by an S_b x n_gt[b] int32 count
- * table per image (beyond 32 regions written only for labels that meet more than
- * 16 regions, and 128 bytes per label besides).  out_host: 3 doubles per image (BR, UE, ASA);
+ * table per image.  out_host: 3 doubles per image (BR, UE, ASA);
  * sums_host (nullable): 4 int64 per image (recovered boundary pixels,
  * ground-truth boundary pixels, the sum of Eq. ue, the sum of Eq. asa).
  * Synchronises `stream`.  Errors: E_INVAL for null or misaligned pointers,

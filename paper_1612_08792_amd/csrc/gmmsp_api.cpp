@@ -1465,53 +1465,52 @@ int gmmsp_connectivity_static(gmmsp_handle* h, const float* lab_dev, const int32
 namespace {
 
 struct MetricSizes {
-  size_t img, clear, wide, brp, total;  // sections of the workspace
-  size_t flag, sums;                    // offsets in the cleared section
+  size_t img, flag, sums, tab, brp, total;  // sections of the workspace
+  size_t clear;                             // bytes to clear from the flags on
   int64_t max_rows;
-  int rows, max_blocks;
+  int rows, max_blocks, sum_stride;
   bool slots;
   std::vector<OverlapImg> ov;
 };
 
-// Cleared: the dense tables of images without slots, the slots, the flags, the sums
-// and the two error words; then the dense tables behind the slots, and the blocks'
-// counts.
+// The image descriptors; cleared: the flags, the sums with the two error words, the
+// tables of images without slots; then the other images' tables and the blocks'
+// counts.  Not larger than 24 bytes per image, 4 S G + 16 S bytes for its labels, 8
+// per block and 32 per image for the sums, each section rounded up to 256.
 static int metric_sizes(const gmmsp_handle* h, const int32_t* n_sp, const int32_t* n_gt, MetricSizes* z) {
   const size_t n_img = (size_t)h->n_img;
-  int64_t tab = 0, wide = 0, flags = 0;
+  int64_t dense = 0, tab = 0, labels = 0;
   int max_w = 0, max_h = 0;
   z->max_rows = 0;
+  z->slots = false;
   z->ov.assign(n_img, OverlapImg{});
   for (int32_t b = 0; b < h->n_img; ++b) {
     const int64_t k = n_sp ? (int64_t)n_sp[b] : (int64_t)h->img[b].nx * h->img[b].ny;
     if (k < 1) return fail(GMMSP_E_INVAL, "image %d: the label count must be >= 1", b);
     if (n_gt[b] < 1) return fail(GMMSP_E_INVAL, "image %d: n_gt must be >= 1", b);
     if (k * n_gt[b] >= ((int64_t)1 << 31)) return fail(GMMSP_E_SIZE, "image %d: labels x n_gt too large", b);
-    const int64_t per = overlap_slots(n_gt[b]);
-    OverlapImg& o = z->ov[b];
-    o = OverlapImg{(int32_t)k, n_gt[b], per ? wide : tab, per ? tab : -1, flags};
-    if (per) {
-      wide += k * n_gt[b];
-      flags += k;
-    }
-    // (slots begin on a cache line)
-    tab += (k * (per ? per : n_gt[b]) + 31) / 32 * 32;
+    const bool slots = overlap_has_slots(n_gt[b]);
+    int64_t& at = slots ? tab : dense;
+    z->ov[b] = OverlapImg{(int32_t)k, n_gt[b], at, labels};
+    at += k * n_gt[b];
+    labels += k;
+    z->slots |= slots;
     z->max_rows = std::max(z->max_rows, k);
     max_w = std::max(max_w, h->img[b].W);
     max_h = std::max(max_h, h->img[b].H);
   }
-  z->slots = flags > 0;
+  for (OverlapImg& o : z->ov)  // (behind the dense ones)
+    if (overlap_has_slots(o.G)) o.tab += dense;
   z->rows = metrics_tile_rows(max_w, max_h, h->n_img);
   z->max_blocks = metrics_max_blocks(max_w, max_h, z->rows);
+  z->sum_stride = metrics_sum_stride(labels, h->n_img);
   z->img = align256(sizeof(OverlapImg) * n_img);
-  z->flag = align256(sizeof(int) * (size_t)tab);
-  z->sums = z->flag + align256(sizeof(int) * (size_t)flags);
-  z->clear = z->sums + align256(sizeof(int64_t) * kMSum * n_img + 2 * sizeof(int));
-  z->wide = align256(sizeof(int) * (size_t)wide);
+  z->flag = align256(sizeof(int) * (size_t)labels);
+  z->sums = align256(sizeof(int64_t) * z->sum_stride * n_img + 2 * sizeof(int));
+  z->tab = align256(sizeof(int) * (size_t)(dense + tab));
+  z->clear = z->flag + z->sums + (sizeof(int) * (size_t)dense + 15) / 16 * 16;
   z->brp = align256(sizeof(int) * 2 * n_img * (size_t)z->max_blocks);
-  z->total = z->img + z->clear + z->wide + z->brp;
-  for (OverlapImg& o : z->ov)
-    if (o.slot >= 0) o.tab += (int64_t)(z->clear / sizeof(int));
+  z->total = z->img + z->flag + z->sums + z->tab + z->brp;
   return GMMSP_OK;
 }
 
@@ -1539,11 +1538,12 @@ int gmmsp_metrics(gmmsp_handle* h, const int32_t* labels_dev, const int32_t* gt_
   if (ws_bytes < z.total) return fail(GMMSP_E_SIZE, "metrics workspace %zu < %zu bytes", ws_bytes, z.total);
   char* base = (char*)ws_dev;
   OverlapImg* d_ov = (OverlapImg*)base;
-  char* clear = base + z.img;
-  int64_t* d_sums = (int64_t*)(clear + z.sums);
-  const size_t n_sums = kMSum * (size_t)h->n_img;
-  const OverlapPtrs T{(int*)clear, (int*)(clear + z.flag), (int*)(d_sums + n_sums), d_sums};
-  int* d_brp = (int*)(clear + z.clear + z.wide);
+  int* d_flag = (int*)(base + z.img);
+  int64_t* d_sums = (int64_t*)(base + z.img + z.flag);
+  int* d_tab = (int*)(base + z.img + z.flag + z.sums);
+  int* d_brp = (int*)(base + z.img + z.flag + z.sums + z.tab);
+  const size_t n_sums = z.sum_stride * (size_t)h->n_img;
+  const OverlapPtrs T{d_tab, d_flag, (int*)(d_sums + n_sums), d_sums, z.sum_stride};
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipMemcpyAsync(d_ov, z.ov.data(), sizeof(OverlapImg) * z.ov.size(),
                                 hipMemcpyHostToDevice, s);
@@ -1559,7 +1559,7 @@ int gmmsp_metrics(gmmsp_handle* h, const int32_t* labels_dev, const int32_t* gt_
   memcpy(err, &sums[n_sums], sizeof(err));
   if (err[0]) return fail(GMMSP_E_INVAL, "a label or region id is outside [0, n_sp) or [0, n_gt)");
   for (int32_t b = 0; b < h->n_img; ++b) {
-    const int64_t* q = sums.data() + kMSum * b;
+    const int64_t* q = sums.data() + (size_t)z.sum_stride * b;
     const double n = (double)h->img[b].W * (double)h->img[b].H;
     out_host[3 * b + 0] = q[1] ? (double)q[0] / (double)q[1] : 1.0;
     out_host[3 * b + 1] = (double)q[2] / n - 1.0;

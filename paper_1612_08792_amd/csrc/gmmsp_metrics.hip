@@ -24,21 +24,32 @@ namespace {
 constexpr int kT = 256;
 constexpr int kR = 2;  // boundary tolerance in pixels (square window)
 
-// The overlaps of an image, OverlapImg:
-//   * G <= kDense: a dense S x G table;
-//   * else, per superpixel, kSlots16 keys (g + 1, 0 empty) and their counts, 128
-//     bytes.  A superpixel that meets more regions than that is flagged and
-//     counted anew by k_m_rescan into its row of a dense table, cleared for the
-//     flagged rows only.
-// The slots are the smaller of the two from 32 regions on.  A dense table of
+// The overlaps of an image, OverlapImg, an S x G table:
+//   * G <= kDense: the dense counts;
+//   * else each superpixel's row begins with kSlots16 keys (g + 1, 0 empty) and
+//     their counts, 128 bytes, and only those are cleared and read.  A superpixel
+//     that meets more regions than that is flagged, and its row cleared whole and
+//     counted anew as a dense one by k_m_rescan.
+// The slots are the shorter of the two from 32 regions on.  A dense table of
 // 8 x 3840x2160 with 10 500 segments and some 2000 regions per image is 680 MB, of
 // which almost all is zero: clearing it took 100 us, reading it 119.
 constexpr int kSlots16 = 16;
 constexpr int kDense = 2 * kSlots16;
 
-__global__ __launch_bounds__(kT) void k_m_clear(int64_t n4, int4* a) {
-  for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n4; i += (int64_t)gridDim.x * kT)
-    a[i] = make_int4(0, 0, 0, 0);
+__device__ __forceinline__ bool has_slots(const OverlapImg& O) { return O.G > kDense; }
+
+// n4 16-byte words from T.flag on (flags, sums, error words, dense tables), and the
+// slots of image blockIdx.y
+__global__ __launch_bounds__(kT) void k_m_clear(const OverlapImg* ov, OverlapPtrs T, int64_t n4) {
+  int4* const a = reinterpret_cast<int4*>(T.flag);
+  const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  const int64_t step = (int64_t)gridDim.x * gridDim.y * kT;
+  for (int64_t i = blk * kT + threadIdx.x; i < n4; i += step) a[i] = make_int4(0, 0, 0, 0);
+  const OverlapImg O = ov[blockIdx.y];
+  if (!has_slots(O)) return;
+  for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < (int64_t)O.K * kDense;
+       i += (int64_t)gridDim.x * kT)
+    T.tab[O.tab + i / kDense * O.G + i % kDense] = 0;
 }
 
 __device__ __forceinline__ int ld_dev(const int* p) {
@@ -48,11 +59,11 @@ __device__ __forceinline__ int ld_dev(const int* p) {
 // n pixels more of superpixel k in region g
 __device__ __forceinline__ void add_overlap(const OverlapImg& O, const OverlapPtrs& T, int k, int g,
                                             int n) {
-  if (O.slot < 0) {
-    atomicAdd(T.tab + O.tab + (int64_t)k * O.G + g, n);
+  int* const row = T.tab + O.tab + (int64_t)k * O.G;
+  if (!has_slots(O)) {
+    atomicAdd(row + g, n);
     return;
   }
-  int* const row = T.tab + O.slot + (int64_t)k * (2 * kSlots16);
   const int h = (int)(((unsigned)g * 2654435761u) >> 28);
   static_assert(kSlots16 == 16, "a hash of four bits");
 #pragma unroll 1
@@ -230,11 +241,11 @@ __global__ __launch_bounds__(kT) void k_m_pix(const ImgDesc* img, const OverlapI
   }
 }
 
-// The dense rows of flagged superpixels cleared, a wave each.
+// The rows of flagged superpixels cleared, a wave each.
 __global__ __launch_bounds__(kT) void k_m_clear_rows(const OverlapImg* ov, OverlapPtrs T) {
   if (T.err[1] == 0) return;
   const OverlapImg O = ov[blockIdx.y];
-  if (O.slot < 0) return;
+  if (!has_slots(O)) return;
   const int lane = threadIdx.x & 63;
   for (int64_t k = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6); k < O.K;
        k += (int64_t)gridDim.x * (kT / 64)) {
@@ -243,14 +254,14 @@ __global__ __launch_bounds__(kT) void k_m_clear_rows(const OverlapImg* ov, Overl
   }
 }
 
-// The pixels of flagged superpixels counted into their dense rows; a lane per
+// The pixels of flagged superpixels counted into their rows; a lane per
 // column of 16 rows.
 __global__ __launch_bounds__(kT) void k_m_rescan(const ImgDesc* img, const OverlapImg* ov,
                                                  OverlapPtrs T, const int32_t* sp,
                                                  const int32_t* gt) {
   if (T.err[1] == 0) return;
   const OverlapImg O = ov[blockIdx.y];
-  if (O.slot < 0) return;
+  if (!has_slots(O)) return;
   const ImgDesc& I = img[blockIdx.y];
   const int W = I.W, H = I.H;
   const int tiles_x = (W + kMW - 1) / kMW;
@@ -277,8 +288,7 @@ __global__ __launch_bounds__(kT) void k_m_rescan(const ImgDesc* img, const Overl
 
 // Sixteen lanes per superpixel: |s_k|, the leaking overlaps, the largest overlap;
 // and the blocks' boundary counts.  A block sums its share of one image and adds the
-// four totals to the image's line of sums (kMSum integers: one cache line, so that
-// the images' atomics do not wait for each other).
+// four totals to the image's sums (T.sum_stride integers apart: see metrics_sum_stride).
 __global__ __launch_bounds__(kT) void k_m_rows(const ImgDesc* img, const OverlapImg* ov,
                                                OverlapPtrs T, const int* br_part, int max_blocks,
                                                int rows) {
@@ -294,9 +304,9 @@ __global__ __launch_bounds__(kT) void k_m_rows(const ImgDesc* img, const Overlap
   }
   for (int64_t k = (int64_t)blockIdx.x * (kT / 16) + threadIdx.x / 16; k < O.K;
        k += (int64_t)gridDim.x * (kT / 16)) {
-    const bool slots = O.slot >= 0 && !T.flag[O.row + k];
+    const bool slots = has_slots(O) && !T.flag[O.row + k];
     const int n = slots ? kSlots16 : O.G;
-    const int* r = T.tab + (slots ? O.slot + k * (2 * kSlots16) + kSlots16 : O.tab + k * O.G);
+    const int* r = T.tab + O.tab + k * O.G + (slots ? kSlots16 : 0);
     const int c0 = t < n ? r[t] : 0, c1 = t + 16 < n ? r[t + 16] : 0;
     int size = c0 + c1, best = max(c0, c1);
     for (int g = 32 + t; g < n; g += 16) {
@@ -323,14 +333,19 @@ __global__ __launch_bounds__(kT) void k_m_rows(const ImgDesc* img, const Overlap
   if (threadIdx.x < 4) {
     int64_t v = 0;
     for (int w = 0; w < kT / 64; ++w) v += red[w][threadIdx.x];
-    if (v) atomicAdd((unsigned long long*)(T.sums + (int64_t)kMSum * b + threadIdx.x),
+    if (v) atomicAdd((unsigned long long*)(T.sums + (int64_t)T.sum_stride * b + threadIdx.x),
                      (unsigned long long)v);
   }
 }
 
 }  // namespace
 
-int64_t overlap_slots(int n_gt) { return n_gt <= kDense ? 0 : 2 * kSlots16; }
+bool overlap_has_slots(int n_gt) { return n_gt > kDense; }
+
+// A cache line per image keeps the images' atomics from waiting for each other (nr
+// of k_m_rows each).  The 96 bytes that it adds per image come out of the workspace
+// that S labels leave: 16 bytes each are allowed for and the flags take 4.
+int metrics_sum_stride(int64_t n_labels, int n_img) { return n_labels >= 16 * (int64_t)n_img + 64 ? 16 : 4; }
 
 int metrics_tile_rows(int max_w, int max_h, int n_img) {
   return (int64_t)m_tiles(max_w, max_h, 16) * n_img <= kSmallTiles ? 4 : 16;
@@ -342,8 +357,10 @@ hipError_t metrics_launch(const DevPtrs& P, int rows, int max_blocks, int64_t ma
                           const OverlapImg* ov, const OverlapPtrs& T, int64_t clear_bytes,
                           const int32_t* sp, const int32_t* gt, int* br_part, hipStream_t s) {
   const int64_t n4 = clear_bytes / 16;
-  hipLaunchKernelGGL(k_m_clear, dim3((unsigned)std::min<int64_t>((n4 + kT - 1) / kT, 8192)), dim3(kT),
-                     0, s, n4, reinterpret_cast<int4*>(T.tab));
+  // some 8192 blocks; at least one per image
+  const int64_t want = std::max((n4 + kT - 1) / kT, slots ? P.n_img * ((max_rows * kDense + kT - 1) / kT) : 1);
+  const unsigned nc = (unsigned)std::max<int64_t>(std::min<int64_t>(want, 8192) / P.n_img, 1);
+  hipLaunchKernelGGL(k_m_clear, dim3(nc, P.n_img), dim3(kT), 0, s, ov, T, n4);
   const dim3 g(max_blocks, P.n_img);
   if (rows == 16)
     hipLaunchKernelGGL(k_m_pix<16>, g, dim3(kT), 0, s, P.img, ov, T, sp, gt, br_part, max_blocks);

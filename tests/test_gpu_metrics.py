@@ -202,3 +202,46 @@ def test_4k_gpu_labels_against_vectorised_counts(dev):
         ue = int(size[k][20 * counts > size[k]].sum())
         assert list(sums[b]) == [int((dist[gb] <= 2).sum()), int(gb.sum()), ue, int(best.sum())]
         assert 0.0 <= vals[b, 1] and 0.0 < vals[b, 2] <= 1.0 and 0.0 <= vals[b, 0] <= 1.0
+
+
+def dense_workspace_bytes(sizes, n_sp, n_gt):
+    """What a caller may allow for: per image 4 + 4 + 8 + 8 bytes of descriptors, an S x G
+    table of int32, two 64-bit values per label, four per image, and two counts per 64 x 16
+    tile of the largest image; each section a multiple of 256."""
+    def up(n):
+        return (n + 255) // 256 * 256
+    n, s = len(sizes), sum(n_sp)
+    tiles = -(-max(w for w, _ in sizes) // 64) * -(-max(h for _, h in sizes) // 16)
+    return (2 * up(4 * n) + up(8 * (n + 1)) + up(8 * n) + up(4 * sum(a * b for a, b in zip(n_sp, n_gt)))
+            + up(8 * n * tiles) + 2 * up(8 * s) + up(32 * n + 4))
+
+
+@pytest.mark.parametrize("n_img,n_sp,n_gt", [(1, 1, 1), (1, 300, 33), (7, 1, 2), (40, 2, 33), (3, 500, 32),
+                                             (5, 150, 1000), (64, 17, 40), (200, 16, 31)])
+def test_workspace_of_the_dense_tables_suffices(dev, n_img, n_sp, n_gt):
+    """Never more than dense tables take, which is what callers have sized for; and the
+    call is right on exactly that much."""
+    from ctypes import byref, c_double, c_int64, c_size_t, c_void_p
+    from paper_1612_08792_amd._lib import check as ok, lib
+    rng = np.random.default_rng(n_img + n_gt)
+    sizes = [(45 + b % 3, 31 + b % 5) for b in range(n_img)]
+    m = GMMSP(sizes, v=4, device=dev)
+    sps = [rng.integers(0, n_sp, (h, w)) for w, h in sizes]
+    gts = [np.minimum(rng.integers(0, n_gt, (h, w)), np.arange(w)[None, :]) for w, h in sizes]
+    ns, ng = np.full(n_img, n_sp, np.int32), np.full(n_img, n_gt, np.int32)
+    need = c_size_t(0)
+    ok(lib().gmmsp_metrics_workspace_bytes(m.handle, c_void_p(ns.ctypes.data),
+                                           c_void_p(ng.ctypes.data), byref(need)))
+    have = dense_workspace_bytes(sizes, ns.tolist(), ng.tolist())
+    say("workspace", need.value, "of", have)
+    assert need.value <= have
+    ws = torch.empty(have, dtype=torch.uint8, device=dev)
+    sp = torch.from_numpy(np.concatenate([s.ravel() for s in sps]).astype(np.int32)).to(dev)
+    gt = torch.from_numpy(np.concatenate([g.ravel() for g in gts]).astype(np.int32)).to(dev)
+    vals, sums = np.zeros((n_img, 3)), np.zeros((n_img, 4), np.int64)
+    ok(lib().gmmsp_metrics(m.handle, c_void_p(sp.data_ptr()), c_void_p(gt.data_ptr()),
+                           c_void_p(ns.ctypes.data), c_void_p(ng.ctypes.data), c_void_p(ws.data_ptr()),
+                           have, c_void_p(vals.ctypes.data), c_void_p(sums.ctypes.data),
+                           c_void_p(m._stream())))
+    for b in range(n_img):
+        check(vals, sums, M.metrics(sps[b], gts[b]), b)
