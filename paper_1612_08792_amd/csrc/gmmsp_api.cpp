@@ -1468,12 +1468,12 @@ struct MetricSizes {
   size_t img, flag, sums, tab, brp, total;  // sections of the workspace
   size_t clear;                             // bytes to clear from the flags on
   int64_t max_rows;
-  int rows, max_blocks, sum_stride;
+  int rows, max_blocks, max_gt, sum_stride;
   bool slots;
   std::vector<OverlapImg> ov;
 };
 
-// The image descriptors; cleared: the flags, the sums with the two error words, the
+// The image descriptors; cleared: the flags, the sums with the error word, the
 // tables of images without slots; then the other images' tables and the blocks'
 // counts.  Not larger than 24 bytes per image, 4 S G + 16 S bytes for its labels, 8
 // per block and 32 per image for the sums, each section rounded up to 256.
@@ -1482,6 +1482,7 @@ static int metric_sizes(const gmmsp_handle* h, const int32_t* n_sp, const int32_
   int64_t dense = 0, tab = 0, labels = 0;
   int max_w = 0, max_h = 0;
   z->max_rows = 0;
+  z->max_gt = 0;
   z->slots = false;
   z->ov.assign(n_img, OverlapImg{});
   for (int32_t b = 0; b < h->n_img; ++b) {
@@ -1489,24 +1490,25 @@ static int metric_sizes(const gmmsp_handle* h, const int32_t* n_sp, const int32_
     if (k < 1) return fail(GMMSP_E_INVAL, "image %d: the label count must be >= 1", b);
     if (n_gt[b] < 1) return fail(GMMSP_E_INVAL, "image %d: n_gt must be >= 1", b);
     if (k * n_gt[b] >= ((int64_t)1 << 31)) return fail(GMMSP_E_SIZE, "image %d: labels x n_gt too large", b);
-    const bool slots = overlap_has_slots(n_gt[b]);
+    const bool slots = overlap_has_slots(k, n_gt[b]);
     int64_t& at = slots ? tab : dense;
-    z->ov[b] = OverlapImg{(int32_t)k, n_gt[b], at, labels};
+    z->ov[b] = OverlapImg{(int32_t)k, n_gt[b], at, h->n_img + labels};
     at += k * n_gt[b];
     labels += k;
     z->slots |= slots;
     z->max_rows = std::max(z->max_rows, k);
+    z->max_gt = std::max(z->max_gt, n_gt[b]);
     max_w = std::max(max_w, h->img[b].W);
     max_h = std::max(max_h, h->img[b].H);
   }
   for (OverlapImg& o : z->ov)  // (behind the dense ones)
-    if (overlap_has_slots(o.G)) o.tab += dense;
+    if (overlap_has_slots(o.K, o.G)) o.tab += dense;
   z->rows = metrics_tile_rows(max_w, max_h, h->n_img);
   z->max_blocks = metrics_max_blocks(max_w, max_h, z->rows);
   z->sum_stride = metrics_sum_stride(labels, h->n_img);
   z->img = align256(sizeof(OverlapImg) * n_img);
-  z->flag = align256(sizeof(int) * (size_t)labels);
-  z->sums = align256(sizeof(int64_t) * z->sum_stride * n_img + 2 * sizeof(int));
+  z->flag = align256(sizeof(int) * (n_img + (size_t)labels));
+  z->sums = align256(sizeof(int64_t) * z->sum_stride * n_img + sizeof(int64_t));
   z->tab = align256(sizeof(int) * (size_t)(dense + tab));
   z->clear = z->flag + z->sums + (sizeof(int) * (size_t)dense + 15) / 16 * 16;
   z->brp = align256(sizeof(int) * 2 * n_img * (size_t)z->max_blocks);
@@ -1549,15 +1551,13 @@ int gmmsp_metrics(gmmsp_handle* h, const int32_t* labels_dev, const int32_t* gt_
                                 hipMemcpyHostToDevice, s);
   if (e == hipSuccess)
     e = metrics_launch(h->P, z.rows, z.max_blocks, z.max_rows, z.slots, d_ov, T, (int64_t)z.clear,
-                       labels_dev, gt_dev, d_brp, s);
-  std::vector<int64_t> sums(n_sums + 1);  // the totals; the error words
+                       z.max_gt, labels_dev, gt_dev, d_brp, s);
+  std::vector<int64_t> sums(n_sums + 1);  // the totals; the error word
   if (e == hipSuccess)
     e = hipMemcpyAsync(sums.data(), d_sums, sizeof(int64_t) * sums.size(), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "gmmsp_metrics");
-  int32_t err[2];
-  memcpy(err, &sums[n_sums], sizeof(err));
-  if (err[0]) return fail(GMMSP_E_INVAL, "a label or region id is outside [0, n_sp) or [0, n_gt)");
+  if (sums[n_sums]) return fail(GMMSP_E_INVAL, "a label or region id is outside [0, n_sp) or [0, n_gt)");
   for (int32_t b = 0; b < h->n_img; ++b) {
     const int64_t* q = sums.data() + (size_t)z.sum_stride * b;
     const double n = (double)h->img[b].W * (double)h->img[b].H;

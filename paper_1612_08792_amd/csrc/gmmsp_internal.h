@@ -334,25 +334,27 @@ hipError_t conn_launch(const ConnPtrs& C, const ImgDesc* img, int n_img, int max
 hipError_t launch_srgb8_to_lab(const uint8_t* rgb, int64_t n, float* lab, hipStream_t s);
 
 // Accuracy measures (gmmsp_metrics.hip).  The overlap counts of an image: K labels,
-// G regions; tab: its table's first entry; row: the first of its labels' flags.
+// G regions; tab: its table's first entry; row: the first of its labels' flags (the
+// flags begin with one per image, set with the first of its labels').
 struct OverlapImg {
   int32_t K, G;
   int64_t tab, row;
 };
-// err[0]: a value out of range; err[1]: a label is flagged
+// err: set if a value is out of range (the low half of a 64-bit word)
 struct OverlapPtrs {
   int *tab, *flag, *err;
   int64_t* sums;            // four totals per image
   int sum_stride;           // 64-bit integers between two images' totals
 };
 
-bool overlap_has_slots(int n_gt);
+bool overlap_has_slots(int64_t n_lab, int n_gt);
 int metrics_sum_stride(int64_t n_labels, int n_img);
 int metrics_tile_rows(int max_w, int max_h, int n_img);
 int metrics_max_blocks(int max_w, int max_h, int rows);  // pixel-pass tiles of the largest image
 // clear_bytes (a multiple of 16) from T.flag on are cleared first, and the slots
 hipError_t metrics_launch(const DevPtrs& P, int rows, int max_blocks, int64_t max_rows, bool slots,
                           const OverlapImg* ov, const OverlapPtrs& T, int64_t clear_bytes,
-                          const int32_t* sp, const int32_t* gt, int* br_part, hipStream_t s);
+                          int max_gt, const int32_t* sp, const int32_t* gt, int* br_part,
+                          hipStream_t s);
 
 }  // namespace gmmsp

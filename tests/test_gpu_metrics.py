@@ -245,3 +245,46 @@ def test_workspace_of_the_dense_tables_suffices(dev, n_img, n_sp, n_gt):
                            c_void_p(m._stream())))
     for b in range(n_img):
         check(vals, sums, M.metrics(sps[b], gts[b]), b)
+
+
+@pytest.mark.parametrize("K,G", [(4, 2000), (1, 5000), (50, 900)])
+def test_coarse_superpixels_over_many_regions(dev, K, G):
+    """Every superpixel meets far more than 16 regions: in compact regions, and in noise,
+    where a 64 x 64 tile has more pairs than its LDS table holds; in a batch with an image
+    none of whose superpixels does."""
+    rng = np.random.default_rng(K)
+    W, H = 190, 131
+    y, x = np.arange(H)[:, None], np.arange(W)[None, :]
+    coarse = np.minimum(y * K // H, K - 1) + 0 * x
+    fine = np.minimum((y // 3) * 64 + x // 3, G - 1)
+    noise = rng.integers(0, G, (H, W))
+    maps = [(coarse, fine), (coarse, noise), (x // 19 + 10 * (y // 14), (x // 50) + 4 * (y // 50))]
+    maps[2] = (maps[2][0], maps[2][1] + 40)
+    n_sp = [K, K, 100]
+    n_gt = [G, G, 60]
+    m = GMMSP([(W, H)] * 3, v=8, device=dev)
+    sp = torch.from_numpy(np.concatenate([a.ravel() for a, _ in maps]).astype(np.int32)).to(dev)
+    gt = torch.from_numpy(np.concatenate([b.ravel() for _, b in maps]).astype(np.int32)).to(dev)
+    for _ in range(2):
+        vals, sums = m.metrics(sp, gt, n_gt, n_sp=n_sp)
+        for b, (s, g) in enumerate(maps):
+            check(vals, sums, M.metrics(s, g), b)
+
+
+@pytest.mark.parametrize("n_gt", [128, 129, 512, 513])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 20])
+def test_regions_at_the_limits_of_the_forms(dev, n_gt, n):
+    """64 labels: dense rows for up to 128 and for more than 512 regions, 16 slots per
+    superpixel between, recounted where a superpixel meets more; rows of up to 256 counts
+    by 16 lanes, longer ones by a block."""
+    rng = np.random.default_rng(1000 * n + n_gt)
+    maps = [striped_regions(W, H, n, n_gt, rng) for W, H in [(129, 65), (63, 17)]]
+    maps.append(striped_regions(70, 40, 18, 300, rng))
+    sizes = [(s.shape[1], s.shape[0]) for s, _ in maps]
+    m = GMMSP(sizes, v=4, device=dev)
+    sp = torch.from_numpy(np.concatenate([s.ravel() for s, _ in maps]).astype(np.int32)).to(dev)
+    gt = torch.from_numpy(np.concatenate([g.ravel() for _, g in maps]).astype(np.int32)).to(dev)
+    for _ in range(2):
+        vals, sums = m.metrics(sp, gt, [n_gt, n_gt, 300], n_sp=[64] * 3)
+        for b, (s, g) in enumerate(maps):
+            check(vals, sums, M.metrics(s, g), b)
