@@ -524,9 +524,9 @@ __global__ __launch_bounds__(64 * WAVES) void k_seg_assign(const ImgDesc* img, c
       }
       ++cnt;
       // (the product is exact in FP32, and below 2^31 so is its rounding there; larger
-      // colours are rounded in FP64 and added by themselves)
-      float big = fmaxf(fmaxf(fabsf(col[k][0]), fabsf(col[k][1])), fabsf(col[k][2]));
-      if (big < 2047.f) {
+      // colours and NaN, which compares false, are rounded in FP64 and added by
+      // themselves)
+      if (fabsf(col[k][0]) < 2047.f && fabsf(col[k][1]) < 2047.f && fabsf(col[k][2]) < 2047.f) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) q[c] += (double)rintf(col[k][c] * 0x1p20f);
       } else {

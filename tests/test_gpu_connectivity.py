@@ -318,3 +318,26 @@ def test_4k_gpu_labels_properties(dev):
         assert np.all(4 * sizes >= g.vx * g.vy)
         assert np.all(Oq.ravel()[vals] == vals)                           # ids are own pixels
         assert counts[b][2] == counts[b][0] - counts[b][3]
+
+
+@pytest.mark.parametrize("n_img", [1, 600])
+def test_nan_colour_counts_for_itself_alone(dev, n_img):
+    """A NaN in one channel of a pixel adds nothing to its segment's sum of that channel,
+    and takes nothing from the other pixels' : the same output as with a 0 in its place.
+    Both forms of the segment pass (up to 512 tiles, and more)."""
+    lab = np.full((32, 64, 3), 50.0, np.float32)
+    labels = np.zeros((32, 64), np.int64)
+    labels[:, 34:] = 1
+    lab[:, 34:, 0] = 74.0
+    labels[:, 30:34] = 0
+    labels[14:16, 33:35] = 2                        # 4 pixels between the two, nearer to label 0
+    lab[14:16, 33:35, 0] = 60.0
+    zero = lab.copy()
+    lab[::16, :33, 0] = np.nan                      # the first pixel of each lane's rows
+    zero[::16, :33, 0] = 0.0
+    want, _, _ = run_gpu(dev, [(labels, zero)] * n_img, 8)
+    ref, _ = C.enforce_connectivity(labels, zero, 8, 8)
+    assert np.array_equal(want[0], ref)
+    got, _, _ = run_gpu(dev, [(labels, lab)] * n_img, 8)
+    for b in range(n_img):
+        assert np.array_equal(got[b], ref), b
