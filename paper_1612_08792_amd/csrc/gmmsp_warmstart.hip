@@ -102,16 +102,16 @@ __global__ __launch_bounds__(256) void k_ws_features(DevPtrs P, const float* __r
     for (int q = lane; q < n; q += 64) {
       const float* px = base + 3 * ((int64_t)row * W + col);
       const float c[3] = {px[0] - r0, px[1] - r1, px[2] - r2};
-      const float lf = col < hx ? 1.f : 0.f, rt = col >= vx - hx ? 1.f : 0.f;
-      const float tp = row < hy ? 1.f : 0.f, bt = row >= vy - hy ? 1.f : 0.f;
+      const bool lf = col < hx, rt = col >= vx - hx, tp = row < hy, bt = row >= vy - hy;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         s[j] += c[j];
         s[3 + j] = fmaf(c[j], c[j], s[3 + j]);
-        s[6 + j] = fmaf(c[j], lf, s[6 + j]);
-        s[9 + j] = fmaf(c[j], rt, s[9 + j]);
-        s[12 + j] = fmaf(c[j], tp, s[12 + j]);
-        s[15 + j] = fmaf(c[j], bt, s[15 + j]);
+        // (selected, not multiplied by 0 or 1: c may not be finite)
+        s[6 + j] += lf ? c[j] : 0.f;
+        s[9 + j] += rt ? c[j] : 0.f;
+        s[12 + j] += tp ? c[j] : 0.f;
+        s[15 + j] += bt ? c[j] : 0.f;
       }
       col += dc;
       row += dr;

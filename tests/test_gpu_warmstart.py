@@ -201,6 +201,33 @@ def test_gradients_and_adam_at_split_edges(dev, nx, ny, v):
     np.testing.assert_allclose(params.cpu().numpy(), want, rtol=1e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_a_non_finite_pixel_stays_in_its_halves(dev, bad):
+    """A pixel that is not finite reaches the mean, std and seed features of its cell and
+    the half-cell differences of the halves it lies in, nothing else."""
+    v = 9
+    rng = np.random.default_rng(4)
+    lab = rng.uniform(10, 60, (2 * v, 3 * v, 3)).astype(np.float32)
+    clean = lab.copy()
+    lab[v + 4, v + 1, 1] = bad          # cell (1, 1): left half, neither top nor bottom (row 4 of 9)
+    out = []
+    for x in (lab, clean):
+        m = GMMSP([(3 * v, 2 * v)], v=v, device=dev)
+        m.ws_attach()
+        m.ws_features(torch.from_numpy(x.ravel()).to(dev))
+        out.append(m.ws_read("feat"))
+    got, want = out
+    cell = 1 * 3 + 1
+    others = np.arange(6) != cell
+    assert np.array_equal(got[others], want[others])
+    touched = [1, 4, 8, 11]             # channel a: mean, std, seed minus mean, right minus left
+    rest = [j for j in range(16) if j not in touched]
+    assert np.array_equal(got[cell, rest], want[cell, rest])
+    assert not np.isfinite(got[cell, 1]) and not np.isfinite(got[cell, 8])
+    d = got[cell, 11]                   # finite right half minus a left half of `bad`
+    assert np.isnan(d) if np.isnan(bad) else d == -bad
+
+
 @pytest.mark.parametrize("mask", [0x3FF, 0b0001100011])
 def test_apply_and_targets_match_oracle(batch, dev, mask):
     ims, lab, m = batch
