@@ -169,8 +169,13 @@ constexpr int kWsParams = 26026;
 // kept for the last layer) and 4 x 32 bias sums (FP64)
 constexpr size_t kWsPartFloats = (size_t)1024 * 32 * 9 * 32;
 constexpr int kWsSplitW = (32 * 16 + 2 * 32 * 32 + 16 * 32) * 9;
-constexpr int kWsMaxSplits = 336;
-static_assert((size_t)kWsMaxSplits * (kWsSplitW + 2 * 4 * 32) <= kWsPartFloats, "partials");
+// A split sums four chunks of 32 positions in FP32 (more only where 1024 splits do
+// not hold a step's positions).  The partials of 336 splits fit the buffer, so beyond
+// them the splits go in rounds, whose sums are kept in FP64 at the buffer's end.
+constexpr int kWsMaxSplits = 1024;
+constexpr int kWsRound = 336;
+constexpr size_t kWsAcc = (size_t)kWsRound * (kWsSplitW + 2 * 4 * 32);  // (floats)
+static_assert(kWsAcc + 2 * (size_t)kWsParams <= kWsPartFloats, "partials");
 static_assert(kWsParams == GMMSP_WS_NPARAM, "parameter count");
 static_assert(kMaxWidth == GMMSP_MAX_WIDTH, "widest image");
 
@@ -1271,6 +1276,7 @@ int gmmsp_ws_train_step(gmmsp_handle* h, float* params_dev, float* m_dev, float*
   const int nchunks = (p1 - p0 + 31) / 32;
   const int splits = nchunks < 4 * kWsMaxSplits ? (nchunks + 3) / 4 : kWsMaxSplits;
   const int cps = (nchunks + splits - 1) / splits;
+  const int round = std::min(splits, kWsRound);
   hipError_t e = ws_forward_range(h, params_dev, p0, p1, true, s);
   if (e == hipSuccess) e = ws_launch_loss(W.out, W.tgt, W.g4, p0, p1, W.loss_part, s);
   // layer inputs and output gradients; the input gradients from the last layer
@@ -1287,16 +1293,22 @@ int gmmsp_ws_train_step(gmmsp_handle* h, float* params_dev, float* m_dev, float*
     const WsLayer& L = kWs[l];
     T.l[l] = WsGradLayer{gout[l], xin[l], part, nullptr, (int)L.w_off, (int)L.b_off, gc[l], L.cout,
                          9 * L.cin};
-    part += (size_t)splits * gc[l] * 9 * L.cin;
+    part += (size_t)round * gc[l] * 9 * L.cin;
   }
   for (int l = 0; l < 4; ++l)
-    T.l[l].db_part = reinterpret_cast<double*>(W.part + (size_t)splits * kWsSplitW) +
-                     (size_t)l * splits * 32;
-  if (e == hipSuccess) e = ws_launch_dw(T, W.nbr, splits, cps, p0, p1, s);
+    T.l[l].db_part = reinterpret_cast<double*>(W.part + (size_t)round * kWsSplitW) +
+                     (size_t)l * round * 32;
+  T.acc = reinterpret_cast<double*>(W.part + kWsAcc);
   const float b1c = 1.0f - powf(0.9f, (float)step), b2c = 1.0f - powf(0.999f, (float)step);
-  if (e == hipSuccess)
-    e = ws_launch_update(T, splits, scale, W.loss_part, ws_loss_blocks(p0, p1), W.loss_sum, W.grad,
-                         params_dev, m_dev, v_dev, lr, 0.9f, 0.999f, 1e-8f, b1c, b2c, s);
+  for (int s0 = 0; s0 < splits && e == hipSuccess; s0 += round) {
+    const int n = std::min(round, splits - s0);
+    T.first = s0 == 0;
+    T.last = s0 + n == splits;
+    e = ws_launch_dw(T, W.nbr, n, cps, p0 + s0 * cps * 32, p1, s);
+    if (e == hipSuccess)
+      e = ws_launch_update(T, n, scale, W.loss_part, ws_loss_blocks(p0, p1), W.loss_sum, W.grad,
+                           params_dev, m_dev, v_dev, lr, 0.9f, 0.999f, 1e-8f, b1c, b2c, s);
+  }
   if (e == hipSuccess && loss_host) {
     double ls = 0.0;
     e = hipMemcpyAsync(&ls, W.loss_sum, sizeof(double), hipMemcpyDeviceToHost, s);

@@ -287,13 +287,16 @@ struct WsGradLayer {
 };
 struct WsGradTab {
   WsGradLayer l[4];
+  double* acc;              // the sums of the rounds so far, per parameter
+  bool first, last;         // round of splits
 };
 hipError_t ws_launch_dw(const WsGradTab& T, const int32_t* nbr, int splits, int cps, int p0, int p1,
                         hipStream_t s);
 int ws_loss_blocks(int p0, int p1);
 hipError_t ws_launch_loss(const float* out, const float* tgt, uint16_t* g4, int p0, int p1,
                           double* loss_part, hipStream_t s);
-// gradients from the partials, the loss sum, and Adam on every parameter
+// gradients from the partials, the loss sum, and in the last round Adam on every
+// parameter
 hipError_t ws_launch_update(const WsGradTab& T, int splits, float scale, const double* loss_part,
                             int n_loss, double* loss_sum, float* grad, float* w, float* m, float* v,
                             float lr, float b1, float b2, float eps, float c1, float c2,

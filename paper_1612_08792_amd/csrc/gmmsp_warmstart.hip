@@ -373,7 +373,8 @@ __global__ __launch_bounds__(kDwThreads) void k_ws_dw(WsGradTab T, const int32_t
 // parameter; the last block adds the loss partials.  Blocks of 64 outputs x 4
 // sums: first the weights of the four layers, then one block per layer for its
 // biases, then the loss.  One thread per output took 191 us in four launches
-// (200 splits one after the other); this form takes 7.9 us with Adam.
+// (200 splits one after the other); this form takes 7.9 us with Adam.  Where the
+// splits come in rounds, a round adds to the sums of those before it.
 __global__ __launch_bounds__(256) void k_ws_update(WsGradTab T, int splits, float scale,
                                                    const double* __restrict__ loss_part, int n_loss,
                                                    double* __restrict__ loss_sum,
@@ -421,7 +422,13 @@ __global__ __launch_bounds__(256) void k_ws_update(WsGradTab T, int splits, floa
     return;
   }
   if (q != 0 || idx < 0) return;
-  const float g = (float)((red[o] + red[64 + o] + red[128 + o] + red[192 + o]) * scale);
+  double sum = red[o] + red[64 + o] + red[128 + o] + red[192 + o];
+  if (!T.first) sum += T.acc[idx];
+  if (!T.last) {
+    T.acc[idx] = sum;
+    return;
+  }
+  const float g = (float)(sum * scale);
   grad[idx] = g;
   const float mi = b1 * m[idx] + (1.f - b1) * g;
   const float vi = b2 * v[idx] + (1.f - b2) * g * g;

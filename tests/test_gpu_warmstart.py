@@ -228,6 +228,44 @@ def test_a_non_finite_pixel_stays_in_its_halves(dev, bad):
     assert np.isnan(d) if np.isnan(bad) else d == -bad
 
 
+def test_gradient_sums_lose_at_most_four_chunks(dev):
+    """102 400 positions.  The FP32 part of a weight gradient's sum is over at most four
+    chunks of 32 positions (1024 splits hold up to 131 072).  One position's output
+    gradient is 2^26, every other's 1/16, all inputs of the last layer are 1: beside 2^26
+    (half an ulp is 4) a chunk of small ones (2.0) is lost whole, so the sum may lack the
+    127 others of the big one's four chunks, 7.94, and be rounded once, by 4."""
+    nx = ny = 320
+    m = GMMSP([(2 * nx, 2 * ny)], v=2, device=dev)
+    m.ws_attach()
+    n = m.n_superpixels
+    assert n == nx * ny
+    m.ws_features(torch.full((4 * n * 3,), 30.0, device=dev))
+    g = np.full(n, 1.0 / 16, np.float64)
+    g[0] = 2.0 ** 26
+    tgt = np.zeros((n, 16), np.float32)
+    tgt[:, 0] = -5.0 * g                # the outputs are 0; the gradient 2 (out - tgt) / 10
+    m.ws_write("tgt", tgt)
+    p = np.zeros(26026, np.float32)
+    p[23104:23136] = 1.0                # the third layer's biases
+    params = torch.from_numpy(p).to(dev)
+    mom, vel = torch.zeros_like(params), torch.zeros_like(params)
+    m.ws_train_step(params, mom, vel, 1, 1e-3)
+    assert np.array_equal(m.ws_read("g4")[:, 0], g.astype(np.float32))
+    assert np.all(m.ws_read("y3") == 1.0)
+    grad = m.ws_read("grad").astype(np.float64) * n
+    dW = grad[23136:23136 + 10 * 9 * 32].reshape(10, 9, 32)
+    # the tap of the position itself sees every position, the others' all but a border;
+    # 2^26 is missing where the tap of position 0 leaves the grid
+    y, x = np.divmod(np.arange(n), nx)
+    for tap in range(9):
+        dy, dx = tap // 3 - 1, tap % 3 - 1
+        ok = (y + dy >= 0) & (y + dy < ny) & (x + dx >= 0) & (x + dx < nx)
+        s = g[ok].sum()
+        assert np.abs(dW[0, tap] - s).max() <= 127 / 16 + 4.0, tap
+    # (the bias sum is FP64 throughout: one rounding)
+    assert abs(grad[26016] - g.sum()) <= 4.0 + 1e-6 * 4.0
+
+
 @pytest.mark.parametrize("mask", [0x3FF, 0b0001100011])
 def test_apply_and_targets_match_oracle(batch, dev, mask):
     ims, lab, m = batch
