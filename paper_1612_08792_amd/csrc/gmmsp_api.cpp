@@ -250,6 +250,30 @@ struct gmmsp_handle {
 
 namespace {
 
+// Is the slot-lane statistics pass of the other covariance models (cells of up to 7 j
+// columns in chunks of rc rows, j set by the widest cell of the batch) the cheaper
+// one?  It costs a lane j rc entries a chunk, also where a narrow cell leaves most of
+// them empty; the pixel-lane pass costs rounds of 64 pixels and, for its 72 to 189
+// sums per lane, some 20 entries' time more per cell.  Fitted to passes of some 70
+// shapes on a full chip: a round is 14 to 17 entries.  A pass of 3x3, full and
+// grayscale models with the pixel-lane form / the slot-lane one, us: cells of 3x300
+// pixels 100 / 120, 150 / 184, 59 / 75; 2x64 141 / 165, 203 / 218, 82 / 99; 2x32
+// 219 / 198, 319 / 257, 126 / 117; 9x9 beside 50x50 238 / 310, 325 / 365, 133 / 184.
+static bool alt_slots_pay(const std::vector<ImgDesc>& imgs, int j, int rc) {
+  double entries = 0.0, rounds = 0.0, cells = 0.0;
+  for (const ImgDesc& d : imgs)
+    for (int last_y = 0; last_y < 2; ++last_y)
+      for (int last_x = 0; last_x < 2; ++last_x) {
+        const int w = last_x ? d.W - (d.ncx - 1) * d.vx : d.vx;
+        const int h = last_y ? d.H - (d.ncy - 1) * d.vy : d.vy;
+        const double n = (double)(last_x ? 1 : d.ncx - 1) * (last_y ? 1 : d.ncy - 1);
+        entries += n * ((h + rc - 1) / rc) * rc * j;
+        rounds += n * (double)(((int64_t)w * h + 63) / 64);
+        cells += n;
+      }
+  return entries <= 13.0 * rounds + 20.0 * cells;
+}
+
 // sum over windows of Eq. Ik along one axis: sum_k (min(n, v(k+2)) - max(0, v(k-1)))
 int64_t window_extent_sum(int64_t n_pixels, int64_t v, int64_t n_seeds) {
   int64_t s = 0;
@@ -336,14 +360,16 @@ int gmmsp_create(int32_t n_images, const gmmsp_params* params, void* workspace_d
   P.wpc = 1;
   P.glanes = 1;
   P.cov_mode = L.cov_mode;
-  // the slot-lane statistics pass covers cells up to 56 pixels wide; otherwise
-  // the pixel-lane pass runs
+  // the slot-lane statistics pass covers cells up to 56 pixels wide (in the other
+  // covariance models where alt_slots_pay); otherwise the pixel-lane pass runs
   int32_t max_vx = 0;
   for (const ImgDesc& d : descs) max_vx = std::max(max_vx, d.vx);
   P.estep = 0;
   if (P.cov_mode == 0 && slots_shape(max_vx, &P.slot_j, &P.slot_rc)) P.estep = 1;
   P.slot_rc_max = P.slot_rc;
-  if (P.cov_mode != 0) (void)slots_shape(max_vx, &P.alt_j, &P.alt_rc);
+  if (P.cov_mode != 0 && slots_shape(max_vx, &P.alt_j, &P.alt_rc) &&
+      !alt_slots_pay(descs, P.alt_j, P.alt_rc))
+    P.alt_j = 0;
 
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipMemcpyAsync((void*)P.img, descs.data(), sizeof(ImgDesc) * n_images,

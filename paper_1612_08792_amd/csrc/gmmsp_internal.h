@@ -138,8 +138,7 @@ struct DevPtrs {
   int32_t slot_j, slot_rc;  // k_slots shape: columns per lane, rows per chunk
   int32_t slot_rc_max;      // the largest rows per chunk of this batch's shape
   int32_t alt_j, alt_rc;    // the other covariance models: shape of their slot-lane pass
-                            // (gmmsp_slots_alt.hip); alt_j 0: cells too wide, one pixel
-                            // per lane
+                            // (gmmsp_slots_alt.hip); alt_j 0: one pixel per lane
 };
 
 // How a per-image log-likelihood L(theta^t) is committed: LL_EM appends it to

@@ -214,3 +214,32 @@ def test_one_step_of_tall_cells(mode, vx, vy):
     th1 = O.mstep(res["z"], g, res["R"], res["pos"], res["theta"], p)
     e = errors(m.get_params(), th1, mode)
     assert max(e) <= 1e-5, e       # the one-step tolerance of every model
+
+
+# narrow cells on both sides of the rule by which the pixel-lane pass takes them, alone and
+# beside wider ones, which set the columns per lane of the whole batch
+@pytest.mark.parametrize("cells", [[(2, 33)], [(2, 64)], [(3, 48)], [(3, 64)], [(8, 300)],
+                                   [(9, 9), (50, 50)], [(9, 9), (14, 14)], [(5, 70), (56, 20), (3, 3)]])
+@pytest.mark.parametrize("mode", [1, 2, 3])
+def test_one_step_of_narrow_and_mixed_cells(mode, cells):
+    p = O.Params(cov_mode=mode)
+    sizes, xs, rows, want = [], [], [], []
+    for b, (vx, vy) in enumerate(cells):
+        W, H = 3 * vx + max(1, vx // 3), 2 * vy + max(1, vy // 3)
+        print("narrow cells, cov_mode", mode, vx, vy, flush=True)
+        im = synth.voronoi_lab(W, H, 5, 4.0, 200 + vx, 4)
+        g = O.make_grid(W, H, vx=vx, vy=vy)
+        res = O.run_em(image_of(im, mode), g, p, max_iters=2)
+        sizes.append((W, H))
+        xs.append(torch.from_numpy(image_of(im, mode)).reshape(-1))
+        rows.append(rows_of(res["theta"], mode))
+        want.append((res["ll_final"], O.mstep(res["z"], g, res["R"], res["pos"], res["theta"], p)))
+    dev = torch.device("cuda:0")
+    m = GMMSP(sizes, v=list(cells), device=dev, cov_mode=mode)
+    m.set_params(np.concatenate(rows))
+    m.em_iterate(torch.cat(xs).contiguous().to(dev), 1)
+    got = m.get_params()
+    for b, (ll, th1) in enumerate(want):
+        assert m.ll_history(b)[0] == pytest.approx(ll, rel=1e-7)
+        e = errors(got[m.sp_slice(b)], th1, mode)
+        assert max(e) <= 1e-5, (b, e)       # the one-step tolerance of every model
