@@ -136,7 +136,11 @@ int plan(int32_t n, const gmmsp_params* params, Layout* L, std::vector<ImgDesc>*
   L->cov_mode = params[0].cov_mode;
   L->theta = o;   o = align256(o + sizeof(double) * theta_row_of(L->cov_mode) * n_sp);
   L->rec = o;     o = align256(o + sizeof(float) * rec_floats_of(L->cov_mode) * kSlots * n_cell);
-  L->part = o;    o = align256(o + sizeof(double) * kPartStride * kMaxWpc * n_cell);
+  // float partials; parameter rows are staged there too
+  static_assert(kThetaRowF * sizeof(double) <= kPartStride * kMaxWpc * sizeof(float) &&
+                kThetaRow3 <= kThetaRowF && kThetaRow <= kThetaRowF && kThetaRowG <= kThetaRowF,
+                "a row per cell");
+  L->part = o;    o = align256(o + sizeof(float) * kPartStride * kMaxWpc * n_cell);
   L->llp = o;     o = align256(o + sizeof(double) * kMaxWpc * n_cell);
   L->n_done = o;  o = align256(o + sizeof(int32_t));
   L->pers = o;    o = align256(o + sizeof(PersistArea));
@@ -443,9 +447,8 @@ int gmmsp_set_params(gmmsp_handle* h, const double* theta_host, void* stream) {
   if (!h || !theta_host) return fail(GMMSP_E_INVAL, "null pointer");
   hipStream_t s = (hipStream_t)stream;
   // stage the rows in the partials area, which the next pass overwrites anyway
+  // (at least as many cells as superpixels, each with room for a row: see plan)
   const size_t bytes = sizeof(double) * theta_row_of(h->P.cov_mode) * (size_t)h->P.n_sp;
-  if (bytes > sizeof(double) * kPartStride * (size_t)h->P.n_cell)
-    return fail(GMMSP_E_SIZE, "staging area too small");
   hipError_t e = hipMemcpyAsync(h->P.part, theta_host, bytes, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = launch_reset_state(h->P, s);
   if (e == hipSuccess) h->t_bound = 0;

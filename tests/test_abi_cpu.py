@@ -159,3 +159,16 @@ def test_colour_front_end_rejects_bad_arguments():
     assert L.gmmsp_srgb8_to_lab(c_void_p(0x1000), 4, c_void_p(0x1004), None) == _lib.GMMSP_E_INVAL
     assert L.gmmsp_srgb8_to_lab(c_void_p(0x1000), -1, c_void_p(0x1000), None) == _lib.GMMSP_E_INVAL
     assert L.gmmsp_srgb8_to_lab(c_void_p(0x1000), 0, c_void_p(0x1000), None) == 0
+
+
+# what the library's first callers allocated: (images, v, cov_mode) -> bytes
+@pytest.mark.parametrize("sizes,v,mode,allowed", [
+    ([(481, 321)], 19, 0, 2055424), ([(481, 321)] * 64, 19, 1, 135939072),
+    ([(481, 321)], 1, 2, 762158080), ([(3840, 2160)] * 32, 28, 0, 1579177472),
+    ([(3840, 2160)] * 4, 28, 2, 212498944), ([(1920, 1080)], 32, 3, 9005312),
+    ([(9, 10), (65, 70)], 9, 0, 368128)])
+def test_workspace_fits_what_callers_hold(sizes, v, mode, allowed):
+    arr = (_lib.GmmspParams * len(sizes))(*[make_params(w, h, 0, v, v, cov_mode=mode) for w, h in sizes])
+    n = c_size_t(0)
+    assert _lib.lib().gmmsp_workspace_bytes(len(sizes), arr, byref(n)) == 0
+    assert n.value <= allowed
