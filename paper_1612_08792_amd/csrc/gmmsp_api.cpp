@@ -361,6 +361,7 @@ int gmmsp_create(int32_t n_images, const gmmsp_params* params, void* workspace_d
   P.n_img = n_images;
   P.n_cell = L.n_cell;
   P.n_sp = L.n_sp;
+  P.cell_px = (int32_t)std::min<int64_t>(L.n_pix / L.n_cell, INT32_MAX / 2);
   P.wpc = 1;
   P.glanes = 1;
   P.cov_mode = L.cov_mode;

@@ -606,7 +606,7 @@ hipError_t launch_label(const DevPtrs& P, const float* lab, int32_t* labels, hip
     const hipError_t e = launch_alt_cells(P, 1, lab, labels, nullptr, s);
     if (e != hipSuccess) return e;
   } else {
-    if (label_waves(P.n_cell) == 4)
+    if (label_waves(P, 128) == 4)
       hipLaunchKernelGGL((k_cells<M_LABEL, 4>), dim3(P.n_cell), dim3(256), 0, s, P, lab, labels,
                          (float*)nullptr);
     else
@@ -619,7 +619,7 @@ hipError_t launch_label(const DevPtrs& P, const float* lab, int32_t* labels, hip
 
 hipError_t launch_export_R(const DevPtrs& P, const float* lab, float* R, hipStream_t s) {
   if (P.cov_mode) return launch_alt_cells(P, 2, lab, nullptr, R, s);
-  if (label_waves(P.n_cell) == 4)
+  if (label_waves(P, 128) == 4)
     hipLaunchKernelGGL((k_cells<M_EXPORT_R, 4>), dim3(P.n_cell), dim3(256), 0, s, P, lab,
                        (int32_t*)nullptr, R);
   else

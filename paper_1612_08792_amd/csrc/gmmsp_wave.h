@@ -176,16 +176,24 @@ __device__ __forceinline__ void store_posteriors(float* st, float* dst, uint32_t
 // ---------------------------------------------------------------------------
 // Labels and posteriors of few cells: the four waves of a block share a cell, in
 // rounds of pixels taken in turn.  A wave per cell leaves SIMDs without a wave
-// below 1024 cells and, some way beyond, too few to hide the loads: the posteriors
-// of 481x321 (400 cells) take 6.7 us, 10.6 with a wave per cell, its labels 6.2 and
-// 8.7; those of 1920x1080 (2500 cells) 21.4 and 25.4, of a grayscale one 19.9 and
-// 28.3.  Beyond 4096 cells a wave each has the chip full (four waves per SIMD): those of
-// 64 uneven images (46 773 cells) take 283 us and would take 298 shared, of 32 x
-// 3840x2160 2.96 ms and 3.19.
+// below 1024 cells and, some way beyond, too few to hide the loads; but a cell of few
+// rounds leaves most of four waves idle.  Labels with a wave each / shared, us: one
+// 481x321 (442 cells, 3 rounds) 9.4 / 9.3, the split ones' posteriors 9.6 / 8.8;
+// 1768 such cells 10.9 / 10.8, 2652 12.7 / 13.4, 3536 14.7 / 15.8; 3234 cells of one
+// round 10.0 / 13.2; of four rounds 1980 12.9 / 12.6, 3960 18.1 / 19.4; of seven 3312
+// 25.3 / 23.7, 4554 29.2 / 29.2.  The other models' rounds are half as long: 3x3
+// block, 3094 cells of six rounds 16.1 / 14.8; 3234 of two 10.5 / 11.7.  Posteriors turn
+// at the same places.  Beyond 4096 cells a wave each has the chip full: posteriors
+// of 64 uneven images (46 773 cells) 283 / 298, of 32 x 3840x2160 2960 / 3190.
 // ---------------------------------------------------------------------------
 constexpr int kSplitCells = 4096;
+constexpr int kSplitPerRound = 2048 / 3;
 
-inline int label_waves(int n_cell) { return n_cell <= kSplitCells ? 4 : 1; }
+// round: pixels that a wave takes in one round
+inline int label_waves(const DevPtrs& P, int round) {
+  const int rounds = (P.cell_px + round - 1) / round;
+  return rounds > 1 && P.n_cell <= kSplitCells && P.n_cell / kSplitPerRound < rounds ? 4 : 1;
+}
 
 // A pixel's log-likelihood term (log2 units) on a 2^-22 grid: the integer-valued
 // FP64 sums of these are exact, so L does not depend on how the pixels are dealt.

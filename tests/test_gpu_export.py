@@ -77,3 +77,32 @@ def test_shared_cells_match_one_wave(size, v, mode):
     assert np.array_equal(l2.reshape(n, -1), np.repeat(l1.reshape(1, -1), n, 0))
     assert np.array_equal(ll2, np.repeat(ll1, n)) and np.isfinite(ll1).all()
     assert np.array_equal(r2, np.repeat(r1, n, 0))
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+@pytest.mark.parametrize("size,v", [((95, 57), (19, 19)), ((40, 31), (10, 10)), ((84, 60), (28, 27))])
+def test_shared_cells_on_both_sides_of_the_rule(size, v, mode):
+    """Whether four waves share a cell depends on the cells of the batch and on the rounds
+    of 128 pixels (64 in the other models) of a cell: the largest batch that shares
+    them and the next give every image the labels, L and posteriors of its own."""
+    W, H = size
+    dev = torch.device("cuda:0")
+    m = GMMSP([(W, H)], v=v, device=dev, cov_mode=mode)
+    g = m.grids[0]
+    per = g.ncx * g.ncy
+    rounds = -(-(W * H // per) // (128 if mode == 0 else 64))
+    n = min(682 * rounds, 4097) // per
+    rng = np.random.default_rng(W * 1000 + H)
+    x = torch.from_numpy(rng.uniform(0, 60, W * H * m.channels).astype(np.float32)).to(dev)
+    got = []
+    for k in (1, n - 1, n, n + 1):
+        print("shared cells", size, v, "cov_mode", mode, "batch of", k, flush=True)
+        h, data = GMMSP([(W, H)] * k, v=v, device=dev, cov_mode=mode), x.repeat(k)
+        h.init_seeds(data)
+        labels, ll = h.label(data)
+        got.append((labels.cpu().numpy().reshape(k, -1), np.asarray(ll),
+                    h.export_responsibilities(data).cpu().numpy().reshape(k, -1)))
+    for labels, ll, R in got[1:]:
+        assert np.array_equal(labels, np.broadcast_to(got[0][0], labels.shape))
+        assert np.array_equal(ll, np.broadcast_to(got[0][1], ll.shape))
+        assert np.array_equal(R, np.broadcast_to(got[0][2], R.shape))
