@@ -1433,7 +1433,6 @@ static int connectivity_run(gmmsp_handle* h, const float* lab_dev, const int32_t
   int** seg[13] = {&C.seg_root, &C.seg_img, &C.size0, &C.size, &C.ccnt, &C.coff, &C.cursor,
                    &C.list, &C.poff, &C.cpar, &C.mpar, &C.next, &C.tail};
   for (int i = 0; i < 13; ++i) *seg[i] = (int*)take(z.seg);
-  C.dist = (unsigned long long*)C.next;  // next and tail, z.seg bytes each, are adjacent
   C.colsum = (unsigned long long*)take(z.colsum);
   C.side = (int*)take(z.side);
   hipError_t e = conn_launch(C, h->P.img, h->n_img, z.max_tiles, lab_dev, labels_dev,

@@ -892,10 +892,6 @@ __device__ __forceinline__ int list_pixel(int where, int u, const int* plist) {
   return where >= 0 ? plist[where + u] : ~where;
 }
 
-__device__ __forceinline__ bool key_less(const int* size0, int a, int b) {
-  return size0[a] < size0[b] || (size0[a] == size0[b] && a < b);
-}
-
 // Clusters: the procedure in rounds, all of a cluster's sources at once.
 //
 // A source's visit reads its own pixels and size and the owners of its
@@ -995,6 +991,9 @@ struct MergePtrs {
   const int *seg_img, *list, *lsize, *lpix, *plist, *segid;
   const double* mean;
   int *ccnt, *coff, *mpar;
+  // the block merges with the state in memory
+  const int *size0, *poff, *seg_root;
+  int *cpar, *link, *tail, *work0, *work1;
 };
 
 // One cluster (root r) by the T threads of a team, t = 0 .. T - 1.  False, with
@@ -1210,111 +1209,234 @@ __global__ __launch_bounds__(64) void k_merge_wave(MergePtrs M, int* cnt, const 
   }
 }
 
-// The clusters left over, a block each: in LDS if they fit, else with the state
-// in memory: the owners in mpar, the sizes, bd and bk per segment (bk -1: must
-// wait), a source undecided while cpar holds its cluster root.  A cluster's own
-// ccnt and coff are read before its segments' entries of them serve as sizes and
-// bk.
+// The clusters left over, a block each: in LDS if they fit, else with the state in
+// memory and lists of the sources to look at.
+//
+// A source that some undecided owner of a neighbour precedes waits for that one:
+// nothing else can make it ready.  It is entered in that owner's list of waiters and
+// looked at again when the owner is decided, so a source is looked at as often as it
+// meets another one to wait for (3.4 times in noise), and a round costs what changed in
+// it.  (With passes over all entries in every round, noise, of which a round decides
+// some ten sources, took 1.7 s for 192 x 192 pixels, 0.46 s one source after the
+// other; it takes 46 ms.)  A source that has grown to a quarter of the desired size will
+// do nothing at its turn, so it is decided at once.  Every undecided source is in
+// the next list or waits for an undecided one that precedes it; the first of all
+// waits for none, so every round decides a source.
+//
+// Per segment: size in ccnt; head, the first waiter (kNoWaiter, or kDecided), in
+// coff; the next waiter in cpar (a large segment's is -1); the segments merged into a
+// source are linked from it by link, tail the last of them.  A cluster's own ccnt and
+// coff are read before its segments' entries of them serve for this.  Owners are
+// changed between barriers that no look-up crosses, and two sources decided
+// between the same ones do not own neighbours of each other.
 constexpr int kHugeT = 1024;
+constexpr int kNoWaiter = -1, kDecided = -2, kLastWaiter = INT32_MAX;
+constexpr int kWide = 128;      // sources in a list from which on a lane takes one each
+constexpr int kLanePixels = 8;  // of up to so many pixels; a wave takes a larger one
 
-__global__ __launch_bounds__(kHugeT) void k_merge_block(MergePtrs M, int* cpar, const int* size0,
-                                                        unsigned long long* bd, const int* cnt,
-                                                        const int* rest) {
+// a source's look at its neighbours
+struct Look {
+  int best = -1, blocker = -1;
+  double bd = 0.0;
+};
+
+// current owner of segment nb, the walk shortened for the next one (no owner
+// changes meanwhile)
+__device__ __forceinline__ int owner_of(int* mpar, int nb) {
+  const int u = ld_dev(mpar + nb);
+  const int t = m_find(mpar, u);
+  if (t != u) st_dev(mpar + nb, t);
+  return t;
+}
+
+// neighbour k of pixel j (of member m) for source s, colour ms
+__device__ __forceinline__ void look_at(const MergePtrs& M, const ImgDesc& I, int off, int s, int key,
+                                        const double* ms, int m, int j, int k, Look& L) {
+  const int W = I.W, H = I.H;
+  const int x = j % W, y = j / W;
+  const bool in = k == 0 ? y > 0 : k == 1 ? y + 1 < H : k == 2 ? x > 0 : x + 1 < W;
+  if (!in) return;
+  const int nb = M.segid[off + j + (k == 0 ? -W : k == 1 ? W : k == 2 ? -1 : 1)];
+  if (nb == m) return;
+  const int o = owner_of(M.mpar, nb);
+  if (o == s) return;
+  if (ld_dev(M.cpar + o) != -1 && ld_dev(M.coff + o) != kDecided) {
+    const int ko = M.size0[o];
+    if (ko < key || (ko == key && o < s)) {
+      L.blocker = o;
+      return;
+    }
+  }
+  const double d = colour_dist2(ms, M.mean + 3 * (int64_t)o);
+  if (L.best < 0 || d < L.bd || (d == L.bd && o < L.best)) {
+    L.best = o;
+    L.bd = d;
+  }
+}
+
+__device__ __forceinline__ int seg_pixel(const MergePtrs& M, int m, int u) {
+  const int p = M.poff[m];
+  return p >= 0 ? M.plist[p + u] : M.seg_root[m];
+}
+
+// one lane
+__device__ Look look_lane(const MergePtrs& M, const ImgDesc& I, int off, int s) {
+  Look L;
+  const int key = M.size0[s];
+  const double* m3 = M.mean + 3 * (int64_t)s;
+  const double ms[3] = {m3[0], m3[1], m3[2]};
+  for (int m = s; m >= 0 && L.blocker < 0; m = ld_dev(M.link + m)) {
+    const int np = M.size0[m];
+    for (int u = 0; u < np && L.blocker < 0; ++u) {
+      const int j = seg_pixel(M, m, u) - off;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) look_at(M, I, off, s, key, ms, m, j, k, L);
+    }
+  }
+  return L;
+}
+
+// the whole wave; s and the result are the same in every lane
+__device__ Look look_wave(const MergePtrs& M, const ImgDesc& I, int off, int s) {
+  Look L;
+  const int lane = threadIdx.x & 63;
+  const int key = M.size0[s];
+  const double* m3 = M.mean + 3 * (int64_t)s;
+  const double ms[3] = {m3[0], m3[1], m3[2]};
+  int m = s;
+  while (m >= 0) {
+    // up to sixteen members of up to 16 pixels, four lanes each, then a larger one
+    int mine = -1, large = -1;
+    for (int c = 0; c < 16 && m >= 0 && large < 0; ++c) {
+      if (M.size0[m] > 16) large = m;
+      else if (c == lane >> 2) mine = m;
+      m = ld_dev(M.link + m);
+    }
+    if (mine >= 0) {
+      const int np = M.size0[mine];
+      for (int u = 0; u < np; ++u)
+        look_at(M, I, off, s, key, ms, mine, seg_pixel(M, mine, u) - off, lane & 3, L);
+    }
+    if (large >= 0) {
+      const int n4 = 4 * M.size0[large];
+      for (int u = lane; u < n4; u += 64)
+        look_at(M, I, off, s, key, ms, large, seg_pixel(M, large, u >> 2) - off, u & 3, L);
+    }
+    const unsigned long long blocked = __ballot(L.blocker >= 0);
+    if (blocked) {
+      L.blocker = __shfl(L.blocker, __ffsll(blocked) - 1, 64);
+      return L;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const double od = __shfl_xor(L.bd, o, 64);
+    const int ob = __shfl_xor(L.best, o, 64);
+    if (ob >= 0 && (L.best < 0 || od < L.bd || (od == L.bd && ob < L.best))) {
+      L.best = ob;
+      L.bd = od;
+    }
+  }
+  return L;
+}
+
+// one cluster (root r, n sources from place l0 of the list on), the whole block
+__device__ void merge_lists(const MergePtrs& M, int r, int n, int l0) {
+  __shared__ int n_next;
+  const int t = threadIdx.x, lane = t & 63;
+  const ImgDesc& I = M.img[M.seg_img[r]];
+  const int off = (int)I.pix_off;
+  const int64_t desired = (int64_t)I.vx * I.vy;
+  int* const size = M.ccnt;
+  int* const head = M.coff;
+  for (int q = t; q < n; q += kHugeT) {
+    const int s = M.list[l0 + q];
+    st_dev(size + s, M.lsize[l0 + q]);
+    st_dev(head + s, kNoWaiter);
+    st_dev(M.link + s, -1);
+    st_dev(M.tail + s, s);
+  }
+  if (t == 0) n_next = 0;
+  __syncthreads();  // (the places of lpix serve as a list from here on)
+  const int* src = M.list + l0;
+  int* dst = M.work0 + l0;
+  int cnt = n;
+  // a decided source's waiters go to the next list
+  auto release = [&](int w) {
+    while (w >= 0 && w != kLastWaiter) {
+      const int nx = ld_dev(M.cpar + w);
+      st_dev(dst + atomicAdd(&n_next, 1), w);
+      w = nx;
+    }
+  };
+  for (int round = 0; cnt > 0 && round < n; ++round) {
+    const bool wide = cnt > kWide;
+    const int per = wide ? kHugeT : kHugeT / 64;
+    for (int base = 0; base < cnt; base += per) {
+      // this lane's source (of a wave's one source: lane 0's)
+      const int q = base + (wide ? t : t >> 6);
+      int s = q < cnt ? ld_dev(src + q) : -1;
+      if (s >= 0 && ld_dev(head + s) == kDecided) s = -1;
+      Look L;
+      if (wide) {
+        const int np = s >= 0 ? ld_dev(size + s) : 0;
+        if (s >= 0 && np <= kLanePixels) L = look_lane(M, I, off, s);
+        for (unsigned long long big = __ballot(np > kLanePixels); big; big &= big - 1) {
+          const int l = __ffsll(big) - 1;
+          const Look B = look_wave(M, I, off, __shfl(s, l, 64));
+          if (lane == l) L = B;
+        }
+      } else if (s >= 0) {  // (the same in the whole wave)
+        L = look_wave(M, I, off, s);
+        if (lane != 0) s = -1;
+      }
+      if (s >= 0 && L.blocker >= 0) {
+        const int w = atomicExch(head + L.blocker, s);
+        st_dev(M.cpar + s, w >= 0 ? w : kLastWaiter);
+        s = -1;
+      }
+      __syncthreads();
+      if (s >= 0) {
+        release(atomicExch(head + s, kDecided));
+        const int o = L.best;
+        if (o >= 0) {
+          st_dev(M.mpar + s, o);
+          if (ld_dev(M.cpar + o) != -1) {  // a source, or one that was: not a large segment
+            const int sz = ld_dev(size + s);
+            const int old = atomicAdd(size + o, sz);
+            if (ld_dev(head + o) != kDecided) {
+              const int ln = atomicExch(M.link + o, s), tl = ld_dev(M.tail + s);
+              st_dev(M.link + tl, ln);
+              if (ln < 0) st_dev(M.tail + o, tl);
+            }
+            if (4LL * old < desired && 4LL * (old + sz) >= desired)
+              release(atomicExch(head + o, kDecided));
+          }
+        }
+      }
+      __syncthreads();
+    }
+    cnt = n_next;
+    src = dst;
+    dst = (dst == M.work0 + l0 ? M.work1 : M.work0) + l0;
+    __syncthreads();  // every thread has read n_next
+    if (t == 0) n_next = 0;
+    __syncthreads();
+  }
+  // the walks shortened for the output
+  for (int q = t; q < n; q += kHugeT) owner_of(M.mpar, M.list[l0 + q]);
+}
+
+__global__ __launch_bounds__(kHugeT) void k_merge_block(MergePtrs M, const int* cnt, const int* rest) {
   __shared__ ClusterLds<1024, 4608> S;
   const int nr = cnt[N_BLOCK];
-  const int* segid = M.segid;
-  const int* plist = M.plist;
-  const double* mean = M.mean;
-  int* const mpar = M.mpar;
-  int* const size = M.ccnt;
-  int* const bk = M.coff;
   for (int c = blockIdx.x; c < nr; c += gridDim.x) {
     const int r = rest[c];
     if (merge_rounds<kHugeT>(S, threadIdx.x, r, M)) continue;
     const int n = M.ccnt[r], l0 = M.coff[r];
-    const int* v = M.list + l0;
-    const int* vsize = M.lsize + l0;
-    const int* vpix = M.lpix + l0;
-    const ImgDesc& I = M.img[M.seg_img[r]];
-    const int W = I.W, H = I.H;
-    const int off = (int)I.pix_off;
-    const int64_t desired = (int64_t)I.vx * I.vy;
     __syncthreads();  // every thread has read n and l0
-    for (int q = threadIdx.x; q < n; q += kHugeT) st_dev(size + v[q], vsize[q]);
-    while (true) {
-      int any = 0;
-      for (int q = threadIdx.x; q < n; q += kHugeT) {
-        const int s = v[q];
-        if (ld_dev(cpar + s) != r) continue;
-        __hip_atomic_store(bd + s, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        st_dev(bk + s, INT32_MAX);
-        any = 1;
-      }
-      if (!__syncthreads_or(any)) break;
-      for (int pass = 0; pass < 2; ++pass) {
-        // neighbour k of pixel j of member m, whose current owner is s
-        auto entry = [&](int m, int s, int j, int k, unsigned long long best) {
-          const int x = j % W, y = j / W;
-          const bool in = k == 0 ? y > 0 : k == 1 ? y + 1 < H : k == 2 ? x > 0 : x + 1 < W;
-          if (!in) return;
-          const int nb = segid[off + j + (k == 0 ? -W : k == 1 ? W : k == 2 ? -1 : 1)];
-          if (nb == m) return;
-          const int o = m_find(mpar, nb);
-          if (o == s) return;
-          if (ld_dev(cpar + o) == r && key_less(size0, o, s)) {
-            st_dev(bk + s, -1);  // (the smallest value: no minimum raises it again)
-            return;
-          }
-          const unsigned long long d = (unsigned long long)__double_as_longlong(
-              colour_dist2(mean + 3 * (int64_t)s, mean + 3 * (int64_t)o));
-          if (pass == 0)
-            atomicMin(bd + s, d);
-          else if (d == best)
-            atomicMin(bk + s, o);
-        };
-        // a lane per member; the pixels of a larger member over the whole wave
-        constexpr int kOwn = 2;
-        const int lane = threadIdx.x & 63;
-        for (int q0 = threadIdx.x - lane; q0 < n; q0 += kHugeT) {
-          int m = -1, s = -1, np = 0, p = 0;
-          unsigned long long best = 0;
-          if (q0 + lane < n) {
-            m = v[q0 + lane];
-            s = m_find(mpar, m);
-            if (ld_dev(cpar + s) == r) {  // undecided
-              np = vsize[q0 + lane];
-              p = vpix[q0 + lane];
-              if (pass) best = __hip_atomic_load(bd + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-          }
-          if (np <= kOwn)
-            for (int u = 0; u < 4 * np; ++u)
-              entry(m, s, list_pixel(p, u >> 2, plist) - off, u & 3, best);
-          for (unsigned long long big = __ballot(np > kOwn); big; big &= big - 1) {
-            const int l = __ffsll(big) - 1;
-            const int mm = __shfl(m, l, 64), ss = __shfl(s, l, 64), pp = __shfl(p, l, 64);
-            const int nn = 4 * __shfl(np, l, 64);
-            const unsigned long long bb = __shfl(best, l, 64);
-            for (int u = lane; u < nn; u += 64)
-              entry(mm, ss, list_pixel(pp, u >> 2, plist) - off, u & 3, bb);
-          }
-        }
-        __syncthreads();
-      }
-      for (int q = threadIdx.x; q < n; q += kHugeT) {
-        const int s = v[q];
-        if (ld_dev(cpar + s) != r) continue;
-        const int o = ld_dev(bk + s);
-        if (o < 0) continue;
-        st_dev(cpar + s, -2);
-        if (o == INT32_MAX || 4LL * ld_dev(size + s) >= desired) continue;
-        st_dev(mpar + s, o);
-        atomicAdd(size + o, ld_dev(size + s));
-      }
-      __syncthreads();
-      for (int q = threadIdx.x; q < n; q += kHugeT) st_dev(mpar + v[q], m_find(mpar, v[q]));
-      __syncthreads();
-    }
+    merge_lists(M, r, n, l0);
+    __syncthreads();  // (n_next is used again)
   }
 }
 
@@ -1443,7 +1565,7 @@ hipError_t conn_launch(const ConnPtrs& C, const ImgDesc* img, int n_img, int max
   // where a block ends in atomics on shared counters, fewer and longer ones
   const dim3 ga(std::min(blocks(n), 1024u));
   const double* mean = reinterpret_cast<const double*>(C.colsum);
-  // (tail: list cursors of the clusters until the block merges' distances)
+  // (tail: list cursors of the clusters until the block merges)
   hipLaunchKernelGGL(k_seg_zero, gs, dim3(kT), 0, s, C.total, n_img, C.size0, C.colsum, C.ccnt,
                      C.cursor, C.tail, cnt, C.counts);
   // (bsum still holds the block offsets of the root ranks here)
@@ -1458,7 +1580,7 @@ hipError_t conn_launch(const ConnPtrs& C, const ImgDesc* img, int n_img, int max
   // the pixel union-find array is free now: it holds the sources' pixel lists
   const dim3 g4(blocks((C.n_pix + 3) / 4));
   hipLaunchKernelGGL(k_px_fill, g4, dim3(kT), 0, s, n, C.segid, C.poff, C.cursor, C.par);
-  // (next: the clustered sources, until the block merges' distances)
+  // (next: the clustered sources, until the block merges' links)
   hipLaunchKernelGGL(k_merge_single, gs, dim3(kT), 0, s, img, C.total, C.seg_img, C.seg_root, C.size0,
                      C.poff, C.par, C.segid, mean, C.cpar, C.mpar, C.next, cnt);
   hipLaunchKernelGGL(k_cl_count, gs, dim3(kT), 0, s, C.next, cnt, C.cpar, C.ccnt);
@@ -1474,12 +1596,13 @@ hipError_t conn_launch(const ConnPtrs& C, const ImgDesc* img, int n_img, int max
   hipLaunchKernelGGL(k_cl_fill, gs, dim3(kT), 0, s, C.next, cnt, C.cpar, C.coff, C.size0, C.poff,
                      C.seg_root, C.tail, C.list, C.size, C.cursor);
   const MergePtrs M{img, C.seg_img, C.list, C.size, C.cursor, C.par, C.segid, mean,
-                    C.ccnt, C.coff, C.mpar};
+                    C.ccnt, C.coff, C.mpar, C.size0, C.poff, C.seg_root, C.cpar, C.next, C.tail,
+                    C.scan, C.cursor};
   hipLaunchKernelGGL(k_merge_team, dim3(std::min(2 * blocks(n), 8192u)), dim3(64), 0, s, M, cnt, team,
                      half, wave);
   hipLaunchKernelGGL(k_merge_wave, dim3(std::min(blocks(n), 3584u)), dim3(64), 0, s, M, cnt, wave, rest);
-  hipLaunchKernelGGL(k_merge_block, dim3(std::min(blocks(n), 256u)), dim3(kHugeT), 0, s, M, C.cpar,
-                     C.size0, C.dist, cnt, rest);
+  // (next and tail are free now, and so is the root-rank array)
+  hipLaunchKernelGGL(k_merge_block, dim3(std::min(blocks(n), 256u)), dim3(kHugeT), 0, s, M, cnt, rest);
   // final segments ranked in id order; each segment's output value (into the
   // working sizes, no longer needed); the output
   if (compact) {

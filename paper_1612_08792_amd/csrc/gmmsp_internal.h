@@ -321,7 +321,6 @@ struct ConnPtrs {
   // (several serve again once their first use is over: see conn_launch)
   int *seg_root, *seg_img, *size0, *size, *ccnt, *coff, *cursor, *list, *poff;
   int *cpar, *mpar, *next, *tail;
-  unsigned long long* dist; // one per segment, over next and tail (adjacent arrays)
   unsigned long long* colsum;  // [n_seg][3] quantised colour sums, then FP64 means
 };
 size_t conn_scan_blocks(int64_t n);

@@ -341,3 +341,50 @@ def test_nan_colour_counts_for_itself_alone(dev, n_img):
     got, _, _ = run_gpu(dev, [(labels, lab)] * n_img, 8)
     for b in range(n_img):
         assert np.array_equal(got[b], ref), b
+
+
+def fragments(kind, S, rng):
+    y, x = np.divmod(np.arange(S * S).reshape(S, S), S)
+    if kind == "noise":
+        return rng.integers(0, 50, (S, S))
+    if kind == "checkers":
+        return (x + y) % 2
+    if kind == "blocks":                       # members of 1 to 25 pixels
+        return (y // 5) * 1000 + x // 5 + np.where(rng.random((S, S)) < 0.2, 7, 0)
+    return np.where(rng.random((S, S)) < 0.6, rng.integers(0, 9, (S, S)), (y // 8) * 100 + x // 8)
+
+
+@pytest.mark.parametrize("kind", ["noise", "checkers", "blocks", "specks"])
+@pytest.mark.parametrize("S,v", [(40, 8), (72, 8), (72, 19)])
+@pytest.mark.parametrize("flat", [False, True])
+def test_clusters_beyond_lds_bit_exact(dev, kind, S, v, flat):
+    """Clusters of more than 1024 sources, where the sources wait for one another in
+    long chains; flat colours, so that every distance ties; two at once beside an image
+    whose clusters are small."""
+    rng = np.random.default_rng(S + v)
+    items = []
+    for b in range(2):
+        lab = np.full((S, S, 3), 40.0) if flat else rng.normal(50, 10, (S, S, 3))
+        items.append((fragments(kind, S, rng), lab.astype(np.float32)))
+    items.append(fragmented(5, 50, 61, v, 0.02))
+    say(kind, S, v, flat)
+    say("largest cluster", small_cluster_sizes(items[0][0], v)[0].max())
+    check_exact(dev, items, v)
+
+
+@pytest.mark.parametrize("kind", ["noise", "checkers"])
+def test_noise_takes_no_longer_than_one_source_at_a_time(dev, kind):
+    """192 x 192 pixels of noise in one cluster: 0.46 to 0.50 s with one source after the
+    other on one thread, 1.7 to 1.9 with passes over the whole cluster in every round."""
+    S, rng = 192, np.random.default_rng(3)
+    m = GMMSP([(S, S)], v=19, device=dev)
+    lab = torch.from_numpy(rng.normal(50, 10, S * S * 3).astype(np.float32)).to(dev)
+    labels = torch.from_numpy(fragments(kind, S, rng).astype(np.int32).ravel()).to(dev)
+    m.connectivity(lab, labels)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    m.connectivity(lab, labels)
+    torch.cuda.synchronize()
+    dt = time.perf_counter() - t0
+    say(kind, dt)
+    assert dt < 0.46
