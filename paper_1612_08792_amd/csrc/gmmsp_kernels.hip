@@ -5,13 +5,14 @@
 // Work decomposition.  The image is cut into v_x x v_y pixel cells (plus the
 // partial remainder column / row).  All pixels of a cell share the same
 // candidate set K_i: the superpixels of the 3 x 3 neighbouring seed cells
-// (Eq. Ik), so one 64-lane wave owns one cell, reads its nine cell-slot records
+// (Eq. Ik), so one 64-lane wave owns one cell (four waves where the schedule or a
+// small batch's labels and exports ask for it), reads its nine cell-slot records
 // with scalar loads, evaluates the E-step of each pixel in registers and keeps
 // the 9 x 13 sufficient statistics of the M-step in registers.  A butterfly
-// reduce-scatter across the wave leaves two totals per lane, written in FP64 as
-// the cell's partials.  Superpixel k then sums the partials of the (at most)
-// nine cells of its window I_k in a fixed order: no atomics, bitwise
-// repeatable.
+// reduce-scatter across the wave leaves two FP32 totals per lane, the cell's
+// partials.  Superpixel k then sums the partials of the (at most) nine cells of its
+// window I_k in FP64 in a fixed order: no atomics, bitwise repeatable.  (Cells of up
+// to 56 columns have the statistics pass of gmmsp_slots.hip.)
 #include "gmmsp_gather.h"
 #include "gmmsp_internal.h"
 #include "gmmsp_wave.h"
@@ -118,9 +119,9 @@ __device__ __forceinline__ float eval_l(const AS4 float* f, float xr, float yr, 
 // E-step of NP pixels per lane against the nine records of the wave's cell:
 // e[p][s] is proportional to R_(i_p, s) (Eq. Rik), sum[p] = sum_s e[p][s], and
 // shift[p] is the log2 offset of e (0 unless all nine densities underflowed).
-// Each record value is read once (scalar load) for all NP pixels; with kLdsOff
-// the offsets (O1, O2, O3, O4, OL) come from the wave's LDS block loff (the
-// statistics pass), otherwise from the records.
+// Each record value is read once (scalar load) for all NP pixels; the offsets (O1,
+// O2, O3, O4, OL) come from the wave's LDS block loff, and from the records again
+// where all nine densities underflow.
 
 // log2 p(z; theta_k) - cmax2 with the five offsets in vector registers
 __device__ __forceinline__ float eval_l_o(const AS4 float* f, float o1, float o2, float oL,
@@ -139,28 +140,23 @@ __device__ __forceinline__ float eval_l_o(const AS4 float* f, float o1, float o2
   return l;
 }
 
-template <int NP, bool kLdsOff = false>
+template <int NP>
 __device__ __forceinline__ void estep_pixels(const AS4 float* rec, size_t rs, const float (&xr)[NP],
                                              const float (&yr)[NP], const float (&L)[NP],
                                              const float (&A)[NP], const float (&B)[NP],
                                              float (&e)[NP][kSlots], float (&sum)[NP],
-                                             float (&shift)[NP], const float* loff = nullptr) {
+                                             float (&shift)[NP], const float* loff) {
 #pragma unroll
   for (int p = 0; p < NP; ++p) sum[p] = 0.f;
 #pragma unroll
   for (int s = 0; s < kSlots; ++s) {
     const AS4 float* f = rec + s * rs;
     float l[NP];
-    if constexpr (kLdsOff) {
-      float o[5];
-      load_offsets(loff, s, o);
+    float o[5];
+    load_offsets(loff, s, o);
 #pragma unroll
-      for (int p = 0; p < NP; ++p)
-        l[p] = eval_l_o(f, o[0], o[1], o[4], o[2], o[3], xr[p], yr[p], L[p], A[p], B[p]);
-    } else {
-#pragma unroll
-      for (int p = 0; p < NP; ++p) l[p] = eval_l(f, xr[p], yr[p], L[p], A[p], B[p]);
-    }
+    for (int p = 0; p < NP; ++p)
+      l[p] = eval_l_o(f, o[0], o[1], o[4], o[2], o[3], xr[p], yr[p], L[p], A[p], B[p]);
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       e[p][s] = __builtin_amdgcn_exp2f(l[p]);
@@ -337,7 +333,7 @@ __global__ __launch_bounds__(256) CELLS_ATTR void k_cells(DevPtrs P, const float
       // 45 vector registers
       int vz = 0;
       asm volatile("" : "+v"(vz));
-      estep_pixels<2, true>(rec, rs, xr, yr, L, A, B, e, sum, shift, woff + vz);
+      estep_pixels<2>(rec, rs, xr, yr, L, A, B, e, sum, shift, woff + vz);
       const float inv[2] = {__builtin_amdgcn_rcpf(sum[0]), v2 ? __builtin_amdgcn_rcpf(sum[1]) : 0.f};
       llacc += __builtin_amdgcn_logf(sum[0]) + shift[0];
       llacc += v2 ? __builtin_amdgcn_logf(sum[1]) + shift[1] : 0.f;
@@ -351,7 +347,7 @@ __global__ __launch_bounds__(256) CELLS_ATTR void k_cells(DevPtrs P, const float
       const float xr[1] = {(float)c1}, yr[1] = {(float)r1};
       const float L[1] = {q1[0]}, A[1] = {q1[1]}, B[1] = {q1[2]};
       float e[1][kSlots], sum[1], shift[1];
-      estep_pixels<1, true>(rec, rs, xr, yr, L, A, B, e, sum, shift, woff);
+      estep_pixels<1>(rec, rs, xr, yr, L, A, B, e, sum, shift, woff);
       const float inv[1] = {__builtin_amdgcn_rcpf(sum[0])};
       llacc += __builtin_amdgcn_logf(sum[0]) + shift[0];
       accumulate_stats<1>(rec, rs, acc, e, inv, xr, yr, L, A, B);
@@ -393,7 +389,7 @@ __global__ __launch_bounds__(256) CELLS_ATTR void k_cells(DevPtrs P, const float
       float e[2][kSlots], sum[2], shift[2];
       int vz = 0;
       asm volatile("" : "+v"(vz));
-      estep_pixels<2, true>(rec, rs, xr, yr, L, A, B, e, sum, shift, woff + vz);
+      estep_pixels<2>(rec, rs, xr, yr, L, A, B, e, sum, shift, woff + vz);
       if constexpr (MODE == M_EXPORT_R) {
         // the wave's pixels lie in consecutive rows of the cell, from lane 0's
         // on: at most 64 rows, so an offset from that row fits 32 bits

@@ -156,6 +156,11 @@ __host__ __device__ inline int m_tiles(int W, int H, int rows) {
 
 __device__ __forceinline__ int clampi(int x, int hi) { return min(max(x, 0), hi); }
 
+// What boundary pixels beside the tile widen to in it, by the two bits of their
+// columns from left to right, four bits each: columns x0, x0 + 1 from x0 - 2 (one)
+// and x0 - 1 (both); columns x0 + 62, x0 + 63 from x0 + 64 (both) and x0 + 65 (one).
+constexpr unsigned kLeft = 0x3310, kRight = 0x3230;
+
 // Overlap counts, and per block the boundary recall counts.  A lane per column of
 // the tile: a row's boundary pixels are one ballot and widening them by two columns
 // a few operations on the mask, so the 5 x 5 test of a row is five masks.  Each lane
@@ -164,10 +169,6 @@ __device__ __forceinline__ int clampi(int x, int hi) { return min(max(x, 0), hi)
 // adds to the overlaps once.  Bound by the issue of the rows' operations and the 8 B
 // per pixel: 8 x 3840x2160 takes 221 us, 269 us with a look-up in each row; 399 us
 // with the boundary map of a 64 x 16 tile in LDS and runs along the rows.
-// What boundary pixels beside the tile widen to in it, by the two bits of their
-// columns from left to right, four bits each: columns x0, x0 + 1 from x0 - 2 (one)
-// and x0 - 1 (both); columns x0 + 62, x0 + 63 from x0 + 64 (both) and x0 + 65 (one).
-constexpr unsigned kLeft = 0x3310, kRight = 0x3230;
 
 template <int R>
 __global__ __launch_bounds__(kT) void k_m_pix(const ImgDesc* img, const OverlapImg* ov,

@@ -243,3 +243,29 @@ def test_one_step_of_narrow_and_mixed_cells(mode, cells):
         assert m.ll_history(b)[0] == pytest.approx(ll, rel=1e-7)
         e = errors(got[m.sp_slice(b)], th1, mode)
         assert max(e) <= 1e-5, (b, e)       # the one-step tolerance of every model
+
+
+@pytest.mark.parametrize("mode", [1, 2, 3])
+def test_gather_forms_of_wide_cells(mode):
+    """Cells wider than the slot-lane pass takes: the statistics of the pixel-lane pass
+    through both forms of the gather."""
+    W, H, v = 120, 7, (57, 3)
+    dev = torch.device("cuda:0")
+    im = synth.voronoi_lab(W, H, 4, 4.0, 12, 4)
+    x1 = torch.from_numpy(image_of(im, mode)).reshape(-1).contiguous().to(dev)
+    n = TEAM_MAX // 4 + 1
+    out = []
+    for k in (1, n):
+        print("gather of wide cells, cov_mode", mode, "batch of", k, flush=True)
+        x = x1.repeat(k)
+        m = GMMSP([(W, H)] * k, v=v, device=dev, cov_mode=mode)
+        assert (m.n_superpixels <= TEAM_MAX) == (k == 1)
+        m.init_seeds(x)
+        rows = m.get_params()
+        rows[:, :2].reshape(k, -1, 2)[:, 0] += 4000.0    # the first seed far away: no mass
+        m.set_params(rows)
+        m.em_iterate(x, 5)
+        out.append(m.get_params().reshape(k, -1, m.theta_row))
+    assert np.isfinite(out[0]).all()
+    for k in (0, n // 2, n - 1):
+        assert np.array_equal(out[1][k], out[0][0])
