@@ -118,7 +118,7 @@ __device__ __forceinline__ int m_find(const int* mpar, int t) {
 // last columns in a side buffer; the tile borders are then joined in global memory
 // from those and from the tiles' first rows.  Roots stay the minimum index of their
 // set throughout.  Bound by the latency of the LDS chains and the 8 B per pixel:
-// 8 x 3840x2160 takes 213 us; 387 us when the waves took rows in turn, so that the
+// 8 x 3840x2160 takes 210 us; 387 us when the waves took rows in turn, so that the
 // links ran from row to row, and every pixel followed them to its root.
 
 constexpr int kTW = 64, kTH = 64;  // tile of the component labelling
@@ -698,7 +698,7 @@ constexpr int kOwnPixels = 4;  // pixels that a thread visits by itself
 // here; otherwise it joins its small neighbours' cluster.  Bound by the gathers
 // of the neighbours' indices and means.  On 8 x 3840x2160 after T = 10 (2.58
 // million small segments, 1.61 million of them alone) it takes
-// 427 us; a pass over all pixels for the clusters and one thread per cluster, with
+// 439 us; a pass over all pixels for the clusters and one thread per cluster, with
 // the lone segments taking the general path, took 536 + 1586 us.
 __global__ __launch_bounds__(kT) void k_merge_single(const ImgDesc* img, const int* n_seg_dev,
                                                      const int* seg_img, const int* seg_root,
@@ -920,7 +920,7 @@ __device__ __forceinline__ int list_pixel(int where, int u, const int* plist) {
 // as fast as one of 512), in LDS or, for a cluster larger still, with the state in
 // memory (a noisy image can be one cluster of a million sources).  On the labels of
 // 8 x 3840x2160 after T = 10 (2.67 million segments, 169 000 clusters of 2 to 852
-// sources) the teams take 337 us, the waves 169 and the blocks 232; 370, 300 and
+// sources) the teams take 299 us, the waves 167 and the blocks 254; 370, 300 and
 // 377 us when every round passed over all entries.  Visiting the sources of a
 // cluster one after the other, on one thread up to 16 sources and then a wave, took
 // 1586 + 12 470 us.

@@ -167,7 +167,7 @@ constexpr unsigned kLeft = 0x3310, kRight = 0x3230;
 // then counts the runs of equal (k, g) down its column (a few in 16 rows, so they
 // are marked first and looked up after) in the block's LDS table, which the block
 // adds to the overlaps once.  Bound by the issue of the rows' operations and the 8 B
-// per pixel: 8 x 3840x2160 takes 221 us, 269 us with a look-up in each row; 399 us
+// per pixel: 8 x 3840x2160 takes 230 us, 269 us with a look-up in each row; 399 us
 // with the boundary map of a 64 x 16 tile in LDS and runs along the rows.
 
 template <int R>

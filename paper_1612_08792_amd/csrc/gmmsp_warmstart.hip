@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void k_ws_nbr(DevPtrs P, int32_t* __restrict__
 // rows minus first h, h = floor(v / 2)).  A wave per cell adds up the 18 sums; the
 // features of a block's four cells are then formed side by side, a thread each: on
 // one lane, after reducing every sum to all lanes, they cost as much as the pixels.
-// Bound by the 12 B per pixel: 8 x 3840x2160 takes 211 us, 340 us before (230 us with
+// Bound by the 12 B per pixel: 8 x 3840x2160 takes 207 us, 340 us before (230 us with
 // four cells per wave one after the other).
 constexpr int kWsIn = 16;
 constexpr int kFeatSums = 18;
